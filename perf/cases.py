@@ -44,29 +44,29 @@ def listed():
     return [
         # The smallest call: a unit-test-sized model, four short sequences.  Launches and host work are all of it.  Its vocabulary is
         # small enough that every pass has its logits, and a caller of this size looks at them.
-        _case("tiny round, logits", model="tiny", batch=4, contexts="uniform16_64", lengths_seed=1001, budgets="k4", logits=True),
+        _case("tiny round logits", model="tiny", batch=4, contexts="uniform16_64", lengths_seed=1001, budgets="k4", logits=True),
         # The end of a rollout: most sequences have finished, the few long ones left are decoded without a drafter.
-        _case("1.5b decode, last few", model="1.5b", batch=6, lo=1024, hi=8192, lengths_seed=11),
+        _case("1.5b decode last few", model="1.5b", batch=6, lo=1024, hi=8192, lengths_seed=11),
         # A training step that wants the log-probabilities of a few verified tokens; odd sizes.
-        _case("1.5b round, logits", model="1.5b", batch=3, lo=200, hi=2000, lengths_seed=12, budgets="k3", logits=True),
+        _case("1.5b round logits", model="1.5b", batch=3, lo=200, hi=2000, lengths_seed=12, budgets="k3", logits=True),
         # Plain sampling of a batch of short responses at the temperature of the paper's runs.
-        _case("1.5b decode, sampled", model="1.5b", batch=24, contexts="pareto512", lengths_seed=13, temperature=0.6),
+        _case("1.5b decode sampled", model="1.5b", batch=24, contexts="pareto512", lengths_seed=13, temperature=0.6),
         # The repository's second workload: uniform short chains over a lognormal batch.
-        _case("1.5b round, batch 64", model="1.5b", batch=64, contexts="lognormal2048", lengths_seed=1002, budgets="k4", accept=0.6),
+        _case("1.5b round batch 64", model="1.5b", batch=64, contexts="lognormal2048", lengths_seed=1002, budgets="k4", accept=0.6),
         # Plain decoding in the middle of a rollout (class "short" of the budget policy: no speculation).
-        _case("7b decode, batch 64", batch=64, contexts="pareto512", lengths_seed=14),
+        _case("7b decode batch 64", batch=64, contexts="pareto512", lengths_seed=14),
         # Stragglers: three sequences left, long contexts, long chains.
-        _case("7b round, stragglers", batch=3, lo=16384, hi=32768, lengths_seed=15, budgets="k16", accept=0.8),
+        _case("7b round stragglers", batch=3, lo=16384, hi=32768, lengths_seed=15, budgets="k16", accept=0.8),
         # The benchmark's headline workload: long-tailed batch, budgets by length quartile.
-        _case("7b round, long-tail batch", batch=128, contexts="mix_1k4k_16k32k", lengths_seed=1003, budgets="quartile"),
+        _case("7b round long-tail batch", batch=128, contexts="mix_1k4k_16k32k", lengths_seed=1003, budgets="quartile"),
         # The benchmark's tail workload: sixteen contexts of 32k to 64k tokens.
-        _case("7b round, 32k-64k contexts", batch=16, contexts="uniform32k_64k", lengths_seed=1004, budgets="k16", accept=0.8),
+        _case("7b round 32k-64k contexts", batch=16, contexts="uniform32k_64k", lengths_seed=1004, budgets="k16", accept=0.8),
         # The benchmark's stochastic workload: a large batch, budgets that grow with the logarithm of the length.
-        _case("7b round, sampled", batch=256, contexts="pareto512", lengths_seed=1005, budgets="loglen", temperature=1.0),
+        _case("7b round sampled", batch=256, contexts="pareto512", lengths_seed=1005, budgets="loglen", temperature=1.0),
         # The start of a rollout: a batch of ordinary prompts.
-        _case("1.5b prefill, prompts", kind="prefill", model="1.5b", batch=32, lo=60, hi=1500, lengths_seed=16),
+        _case("1.5b prefill prompts", kind="prefill", model="1.5b", batch=32, lo=60, hi=1500, lengths_seed=16),
         # Long prompts (re-prefilled contexts after a weight update); the largest case.
-        _case("7b prefill, long", kind="prefill", batch=3, lo=4000, hi=16384, lengths_seed=17),
+        _case("7b prefill long", kind="prefill", batch=3, lo=4000, hi=16384, lengths_seed=17),
     ]
 
 
