@@ -62,6 +62,7 @@ struct das_model {
     size_t gemm_ws_floats = 0;
     uint16_t *part_o = nullptr;      // split-KV partial outputs (fp16, normalised per chunk)
     float *part_ml = nullptr;        // their (m, l) per row
+    float4 *attn_fold = nullptr;     // running sums of the blocks whose attention is taken whole
     size_t part_rows_cap = 0;        // 16-row blocks the partial buffers hold (fixed at load)
     int max_blocks = 0;              // most blocks one pass may have (sequences + extra prompt blocks of a prefill pass)
     unsigned long long *d_kv_sat = nullptr;      // K/V elements that did not fit their container, ever
@@ -153,19 +154,46 @@ static void shrink_pages(das_model *m, int slot, int tokens) {
     while ((int)s.pages.size() > pages_for(tokens)) { m->free_pages.push_back(s.pages.back()); s.pages.pop_back(); }
 }
 
+// How the attention of a pass is cut into work items.  A block with up to 8 row blocks of 16 query rows per KV head is cut
+// into (chunk, KV head) items; its chunk results meet in the merge kernel.  A block with more row blocks (a prompt block, a
+// long draft; attn_rows_kernel, one item per CU at a time) is taken WHOLE -- one item per KV head walks all chunks and writes
+// finished rows, no partials -- when it has one chunk, when its items are at most a quarter longer than an even share of the
+// launch's tiles over the compute units (the launch fills the chip without cutting it; 57 blocks of 36 rows behind 13k tokens,
+// 7B shape: 228 items in one round), or when its partials do not fit the buffers.  Same bits either way.
+// Partials are kept per 16-row block: 16 x D accumulators in the lane order the MFMA leaves them in, and (m, l) per row.
+struct AttnPlan {
+    std::vector<int> first_row;      // per block: its first 16-row block in the partial buffers (taken whole: its place in the fold workspace)
+    std::vector<char> whole;         // per block: taken whole
+    size_t part_rows = 0, items = 0, merge_blocks = 0;
+};
+static int row_blocks(const das_model *m, const PassBlock &b) { return (m->dm.G * b.n + 15) / 16; }
+static AttnPlan attn_plan(const das_model *m, const std::vector<PassBlock> &blocks) {
+    const int chunk_tokens = das_attn_chunk(m->dm.Hkv), Hkv = m->dm.Hkv;
+    AttnPlan pl;
+    size_t tiles = 0;      // of the blocks with many rows
+    int n_whole = 0;
+    for (auto &b : blocks) if (row_blocks(m, b) > 8) tiles += (size_t)((b.start + b.n + DAS_ATTN_TILE - 1) / DAS_ATTN_TILE) * Hkv;
+    const size_t share = tiles / (size_t)das_cu_count();
+    for (auto &b : blocks) {
+        const size_t nrb = (size_t)row_blocks(m, b), nchunk = ((size_t)b.start + b.n + chunk_tokens - 1) / chunk_tokens;
+        const bool whole = nrb > 8 && (nchunk == 1 || (size_t)(b.start + b.n) / DAS_ATTN_TILE * 4 <= share * 5 || pl.part_rows + nchunk * nrb > m->part_rows_cap);
+        pl.first_row.push_back(whole ? n_whole++ : (int)pl.part_rows);
+        pl.whole.push_back(whole);
+        pl.items += (whole ? 1 : nchunk) * Hkv;
+        if (!whole) pl.part_rows += nchunk * nrb;
+        if (!whole && nchunk > 1) pl.merge_blocks += nrb;      // (one chunk: the attention kernel writes the finished rows itself)
+    }
+    return pl;
+}
+
 // Size of a pass before anything is written or changed: ints of the staging block it needs (n_upd page-table
-// updates, n_u uniforms per stream) and 16-row blocks of split-KV partials.  Partials are kept per 16-row block: 16 x D
-// accumulators in the lane order the MFMA leaves them in, and (m, l) per row.
+// updates, n_u uniforms per stream) and 16-row blocks of split-KV partials.
 struct PassSize { size_t stage_ints, part_rows; };
 static PassSize pass_size(const das_model *m, const std::vector<PassBlock> &blocks, size_t n_upd, size_t n_u) {
-    const int chunk_tokens = das_attn_chunk(m->dm.Hkv);
-    size_t T = 0, items = 0, mblk = 0, prow = 0;
-    for (auto &b : blocks) {
-        const size_t nrb = ((size_t)m->dm.G * b.n + 15) / 16, nchunk = ((size_t)b.start + b.n + chunk_tokens - 1) / chunk_tokens;
-        T += b.n; items += nchunk; prow += nchunk * nrb;
-        if (nchunk > 1) mblk += nrb;
-    }
-    return {5 * T + 6 * blocks.size() + 2 * items * m->dm.Hkv + 2 * mblk + 2 * n_upd + 2 * n_u, prow};
+    const AttnPlan pl = attn_plan(m, blocks);
+    size_t T = 0;
+    for (auto &b : blocks) T += b.n;
+    return {5 * T + 6 * blocks.size() + 2 * pl.items + 2 * pl.merge_blocks + 2 * n_upd + 2 * n_u, pl.part_rows};
 }
 static int check_pass_size(const das_model *m, const PassSize &ps) {
     if (ps.stage_ints > m->stage_ints) return DAS_ERR_INVALID;        // over a configured maximum
@@ -185,8 +213,9 @@ static int run_pass(das_model *m, const std::vector<PassBlock> &blocks, const fl
     const int NB = (int)blocks.size();
     int T = 0;
     for (auto &b : blocks) T += b.n;
-    std::vector<int> items[3], mblk;
-    size_t prow = 0;
+    const AttnPlan plan = attn_plan(m, blocks);
+    if (plan.part_rows > m->part_rows_cap) return DAS_ERR_NOMEM;
+    std::vector<int> mblk;
     // ---- pack the metadata
     int *p = m->h_stage;
     int *tok = p; p += T;
@@ -205,16 +234,11 @@ static int run_pass(das_model *m, const std::vector<PassBlock> &blocks, const fl
     for (int b = 0; b < NB; ++b) {
         const PassBlock &pb = blocks[b];
         b_slot[b] = pb.slot; b_start[b] = pb.start; b_n[b] = pb.n; b_row0[b] = r;
-        const int R = dm.G * pb.n, nrb = (R + 15) / 16;
+        const int nrb = row_blocks(m, pb);
         const int nchunk = (pb.start + pb.n + chunk_tokens - 1) / chunk_tokens;
-        b_prow[b] = (int)prow; b_nchunk[b] = nchunk;
-        prow += (size_t)nchunk * nrb;
-        if (nchunk > 1)      // (one chunk: the attention kernel writes the finished rows itself)
+        b_prow[b] = plan.first_row[b]; b_nchunk[b] = nchunk;
+        if (nchunk > 1 && !plan.whole[b])
             for (int rb = 0; rb < nrb; ++rb) { mblk.push_back(b); mblk.push_back(rb); }
-        // two kernel shapes: up to 8 row blocks of 16 query rows per KV head (2 per wave), or up to 16 (4 per wave).
-        // One launch for everything up to 8 blocks lets short sequences fill the tail of the long ones.
-        const int cls = nrb <= 8 ? 1 : 2;
-        for (int c = 0; c < nchunk; ++c) { items[cls].push_back(b); items[cls].push_back(c); }
         for (int j = 0; j < pb.n; ++j, ++r) {
             tok[r] = pb.toks[j]; row_pos[r] = pb.start + j; row_b[r] = b;
             if (pb.want == 2 || (pb.want == 1 && j == pb.n - 1)) {
@@ -223,24 +247,29 @@ static int run_pass(das_model *m, const std::vector<PassBlock> &blocks, const fl
             }
         }
     }
-    if (prow > m->part_rows_cap) return DAS_ERR_NOMEM;
-    // One work item per (sequence, chunk, KV head), longest first over the whole launch so that the short last
-    // chunks fill its tail; among equal lengths one KV head's items run side by side (measured faster than the
-    // heads of one chunk side by side).  Entry: sequence, chunk | head << 20.
-    for (int c = 0; c < 3; ++c) {
-        std::vector<std::pair<int, int>> v;
-        for (int h = 0; h < dm.Hkv; ++h)
-            for (size_t i = 0; i + 1 < items[c].size(); i += 2) v.push_back({items[c][i], items[c][i + 1] | (h << 20)});
-        auto tokens = [&](const std::pair<int, int> &it) {
-            const int total = blocks[it.first].start + blocks[it.first].n;
-            return std::min(total - (it.second & 0xFFFFF) * chunk_tokens, chunk_tokens);
-        };
-        std::stable_sort(v.begin(), v.end(), [&](const std::pair<int, int> &a, const std::pair<int, int> &b) { return tokens(a) > tokens(b); });
-        items[c].resize(2 * v.size());
-        for (size_t i = 0; i < v.size(); ++i) { items[c][2 * i] = v[i].first; items[c][2 * i + 1] = v[i].second; }
+    // Work items, longest first over the whole launch so that short ones fill its tail.  Entry: sequence, chunk | head << 20
+    // (chunk 0xFFFFF: all of them).  Up to 8 row blocks: among equal lengths one KV head's items run side by side (measured
+    // faster than the heads of one chunk side by side); one launch for all of them, so that short sequences fill the tail of
+    // the long ones.  More row blocks: the heads of a block side by side, so that the items of a head, which read nearly the
+    // same keys, sit on the same XCDs (workgroup index mod 8).
+    struct Item { int b, code, tokens; };
+    std::vector<Item> items[2];
+    auto add_items = [&](int b, int h) {
+        const int total = blocks[b].start + blocks[b].n;
+        const bool many = row_blocks(m, blocks[b]) > 8;
+        if (plan.whole[b]) { items[1].push_back({b, 0xFFFFF | (h << 20), total}); return; }
+        for (int c = 0; c < b_nchunk[b]; ++c) items[many ? 1 : 0].push_back({b, c | (h << 20), std::min(total - c * chunk_tokens, chunk_tokens)});
+    };
+    for (int h = 0; h < dm.Hkv; ++h)
+        for (int b = 0; b < NB; ++b) if (row_blocks(m, blocks[b]) <= 8) add_items(b, h);
+    for (int b = 0; b < NB; ++b)
+        for (int h = 0; h < dm.Hkv; ++h) if (row_blocks(m, blocks[b]) > 8) add_items(b, h);
+    int *item_ptr[2];
+    for (int c = 0; c < 2; ++c) {
+        std::stable_sort(items[c].begin(), items[c].end(), [](const Item &a, const Item &b) { return a.tokens > b.tokens; });
+        item_ptr[c] = p;
+        for (auto &it : items[c]) { *p++ = it.b; *p++ = it.code; }
     }
-    int *item_ptr[3];
-    for (int c = 0; c < 3; ++c) { item_ptr[c] = p; std::copy(items[c].begin(), items[c].end(), p); p += items[c].size(); }
     int *mblk_p = p; std::copy(mblk.begin(), mblk.end(), p); p += mblk.size();
     const int n_upd = (int)m->pending_upd.size() / 2;
     int *upd = p; std::copy(m->pending_upd.begin(), m->pending_upd.end(), p); p += 2 * n_upd;
@@ -284,8 +313,8 @@ static int run_pass(das_model *m, const std::vector<PassBlock> &blocks, const fl
         if (qkv_slices > 0) { ProfScope ps(m, KC_ROPE_KV); launch_rope_kv(pm, qkv_slices > 1 ? m->gemm_ws : m->qkv, qkv_slices, m->q_h, m->cs, kl, vl, dm, m->d_kv_sat, st); }
         {
             ProfScope ps(m, KC_ATTN);
-            for (int c = 0; c < 3; ++c)
-                launch_attn(pm, dptr(item_ptr[c]), (int)items[c].size() / 2, 1 << c, m->q_h, kl, vl, m->part_o, m->part_ml, m->attn, dm, st);
+            for (int c = 0; c < 2; ++c)
+                launch_attn(pm, dptr(item_ptr[c]), (int)items[c].size(), c == 1, m->q_h, kl, vl, m->part_o, m->part_ml, m->attn_fold, m->attn, dm, st);
         }
         { ProfScope ps(m, KC_ATTN_MERGE); launch_attn_merge(pm, m->part_o, m->part_ml, m->attn, dm, st); }
         {
@@ -474,16 +503,19 @@ static int load_impl(das_model *m, const uint16_t *wb, uint64_t seed) {
     HIPCHK(hipMemsetAsync(m->d_kv_sat, 0, sizeof(unsigned long long), m->st));
     // ---- split-KV partials, sized here once for every pass the configuration allows.  A block (a sequence's rows in
     // one pass) has at most 16 row blocks of 16 query rows per KV head and one partial per chunk it spans; the chunks of
-    // distinct sequences together are bounded by the KV pool (a chunk is at most half empty per sequence).  A prefill
-    // pass that takes several blocks of ONE prompt is cut to fit this capacity by its caller.
+    // distinct sequences together are bounded by the KV pool (a chunk is at most half empty per sequence).  Several blocks of
+    // ONE prompt in a prefill pass can exceed that: there is room to cut blocks of 16 row blocks until two items per compute
+    // unit are there, and what does not fit is taken whole (attn_plan).
     const int chunk_tokens = das_attn_chunk(c.n_kv_heads);
     m->max_blocks = c.max_seqs + c.max_rows / std::max(1, std::min(256 / dm.G, c.max_rows)) + 1;
     {
         const size_t pool_chunks = (size_t)c.num_pages * DAS_PAGE / chunk_tokens + (size_t)c.max_seqs;
         const size_t per_seq_chunks = (size_t)c.max_ctx / chunk_tokens + 1;
-        m->part_rows_cap = 16 * std::min(pool_chunks, per_seq_chunks * (size_t)c.max_seqs);
+        m->part_rows_cap = 16 * std::max(std::min(pool_chunks, per_seq_chunks * (size_t)c.max_seqs), (size_t)(2 * das_cu_count() / c.n_kv_heads + 1));
         A(m->part_o, m->part_rows_cap * dm.Hkv * 16 * dm.D);
         A(m->part_ml, m->part_rows_cap * dm.Hkv * 32);
+        const int least_rows = 8 * 16 / dm.G + 1;      // of a block with more than 8 row blocks
+        A(m->attn_fold, (size_t)(c.max_rows / least_rows) * dm.Hkv * 16 * dm.D * 4);
     }
     // ---- staging (see pass_size)
     const size_t max_items = (size_t)m->max_blocks * (c.max_ctx / chunk_tokens + 2);

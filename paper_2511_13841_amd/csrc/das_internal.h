@@ -68,7 +68,7 @@ struct PassMeta {
     const int *b_start;    // [NB] first position of the block (= committed length)
     const int *b_n;        // [NB] rows of the block
     const int *b_row0;     // [NB] first row of the block
-    const int *b_prow;     // [NB] base 16-row block in the split-KV partial buffers
+    const int *b_prow;     // [NB] base 16-row block in the split-KV partial buffers (a block taken whole: its place in the fold workspace)
     const int *b_nchunk;   // [NB] split-KV chunks
     const int *mblk;       // [n_mblk][2] (block, 16-row block) pairs: one merge workgroup each per KV head
     int n_mblk;
@@ -168,11 +168,14 @@ void gemm_debug_copies_only(bool on);      // timing mode of das_debug_gemm_time
 int gemm_slices(int K, int *slice_tiles);
 int gemm_slice_group(int slices);                       // eight slices are added as two groups of four (0: one ascending run)
 size_t gemm_ws_floats_needed(int M, int N, int K);     // workspace that lets launch_gemm pick its fastest shape
-// split-KV partial attention for the items of one row-block class, then the merge.  Sequences of one chunk are finished
+int das_cu_count();      // compute units of the current device
+// split-KV partial attention for the items of one row-block class (many_rows: more than 8 row blocks of 16 query rows per KV
+// head, whole blocks among them), then the merge.  Sequences of one chunk are finished
 // by launch_attn itself (their rows go straight to out_frag, bit-equal to what the merge would write), so pm.mblk lists
 // only the row blocks of sequences with two or more chunks.
-void launch_attn(const PassMeta &pm, const int *items, int n_items, int rbw, const f16_t *q_h,
-                 const f16_t *kpool_layer, const f16_t *vpool_layer, uint16_t *part_o, float *part_ml, bf16_t *out_frag,
+// fold: [whole blocks][Hkv][16][D/16][64] running sums of the blocks taken whole.
+void launch_attn(const PassMeta &pm, const int *items, int n_items, bool many_rows, const f16_t *q_h,
+                 const f16_t *kpool_layer, const f16_t *vpool_layer, uint16_t *part_o, float *part_ml, float4 *fold, bf16_t *out_frag,
                  const DasDims &dm, hipStream_t st);
 void launch_attn_merge(const PassMeta &pm, const uint16_t *part_o, const float *part_ml, bf16_t *out_frag,
                        const DasDims &dm, hipStream_t st);

@@ -645,7 +645,7 @@ static void launch_cfg3(int epi, const bf16_t *A, const bf16_t *W, void *C, int 
 }
 
 // Compute units of the current device (asked once; 256 if the query fails).
-static int cu_count() {
+int das_cu_count() {
     static int n_cu = 0;
     if (n_cu == 0) {
         int dev = 0, cus = 0;
@@ -662,7 +662,7 @@ static int cu_count() {
 // K = 3584: 49, 56, 62, 70, 82, 89 us for h = 3 .. 8), and a last round counts in full unless it is nearly empty (measured
 // on 148 column tiles: 296 and 444 workgroups on 256 CUs take the same time).  Ties go to the taller tile.
 static int pick_tile_height(int M, int N, int lo) {
-    const int mb = (M + 31) / 32, tn = (N + 255) / 256, cus = cu_count();
+    const int mb = (M + 31) / 32, tn = (N + 255) / 256, cus = das_cu_count();
     int hb = 8;
     double best = 1e30;
     for (int h = 8; h >= lo; --h) {
@@ -715,7 +715,7 @@ bool launch_gemm(int epi, const bf16_t *A, const bf16_t *W, void *C, int M, int 
         if (M <= 64) launch_one<2, 1, 1, 2, 6, EPI_SILU_FRAG, 2, true>(A, W, C, M, N, K, ldc, st);
         // 193..320 rows: 96x256 tiles on 4 waves of 96x64 (6 MFMAs per 5 fragment reads against 2 per 3), pipelined k loop,
         // seven stages of 22 KiB (six tiles in flight per CU): 121 -> 106 us per layer at T = 272
-        else if (M > 192 && M <= 288 && (N % 512) == 0 && ((N / 512) * 3 + 7) / 8 * 8 <= cu_count())
+        else if (M > 192 && M <= 288 && (N % 512) == 0 && ((N / 512) * 3 + 7) / 8 * 8 <= das_cu_count())
             // 193..288 rows and a width that 96x512 tiles cover in ONE round of workgroups (the 7B gate/up: 3 x 74 = 222
             // tiles on 256 CUs): 4 waves of 96x128, 12 MFMAs per 7 fragment reads, and a third less copied per MFMA than with
             // 96x256 tiles; 105 -> 94 us per layer at T = 272
@@ -724,7 +724,7 @@ bool launch_gemm(int epi, const bf16_t *A, const bf16_t *W, void *C, int M, int 
             // ... or 128x256 tiles (4 waves of 128x64) where those finish in fewer rounds of workgroups times tile height:
             // 320 rows x 17920 packed columns are 280 tiles of 96 rows (a second round for 24 of them on 256 CUs) but 210
             // tiles of 128 rows.  The K order per output element is the same in both.
-            const long nt = (N + 255) / 256, cus = cu_count();
+            const long nt = (N + 255) / 256, cus = das_cu_count();
             const long cost96 = ((M + 95) / 96 * nt + cus - 1) / cus * 96, cost128 = ((M + 127) / 128 * nt + cus - 1) / cus * 128;
             if (cost128 < cost96) launch_one<1, 4, 4, 2, 6, EPI_SILU_FRAG, 2, true, 0, true>(A, W, C, M, N, K, ldc, st);
             else launch_one<1, 4, 3, 2, 7, EPI_SILU_FRAG, 2, true, 0, true>(A, W, C, M, N, K, ldc, st);
@@ -814,7 +814,7 @@ bool launch_gemm(int epi, const bf16_t *A, const bf16_t *W, void *C, int M, int 
     }
     const size_t mn = (size_t)M * N;
     const int group = gemm_slice_group(slices);
-    const bool halves192 = ((M + 191) / 192) * ((N + 191) / 192) * 2 <= cu_count(), halves256 = ((M + 255) / 256) * ((N + 191) / 192) * 2 <= cu_count();
+    const bool halves192 = ((M + 191) / 192) * ((N + 191) / 192) * 2 <= das_cu_count(), halves256 = ((M + 255) / 256) * ((N + 191) / 192) * 2 <= das_cu_count();
     if (M > 512 && group > 0 && ws && ldc == N && (N % 4) == 0 && ws_floats >= 2 * mn && (halves192 || halves256)) {
         // Many rows, long K (the down projection): 128x128 tiles over all of K move 32 KiB per k-tile of 64 and the launch
         // runs at the speed of that copy stream.  When they fit the chip in one round, the two slice groups of the sum go to
@@ -855,7 +855,7 @@ bool launch_gemm(int epi, const bf16_t *A, const bf16_t *W, void *C, int M, int 
         }
         // long K (down projection): 128x128 tiles, k-tiles of 32 in an eight-stage ring (measured 13% faster) -- unless 128x64 tiles
         // still fit one round of workgroups (a narrow output: the 1.5B down projection up to 256 rows, 27.5 -> 22.7 us at 100 rows)
-        else if (K >= 8192 && ((M + 127) / 128) * ((N + 63) / 64) * slices > cu_count())
+        else if (K >= 8192 && ((M + 127) / 128) * ((N + 63) / 64) * slices > das_cu_count())
             launch_one<2, 4, 2, 1, 8, EPI_F32_ROWMAJOR, 2, true, 2>(A, W, ws, M, N, K, N, st, 2 * slice_tiles, slices);
         else launch_one<2, 2, 2, 1, 3, EPI_F32_ROWMAJOR, 4, true, 2>(A, W, ws, M, N, K, N, st, slice_tiles, slices);
         const size_t mn4 = mn / 4;
@@ -871,7 +871,7 @@ bool launch_gemm(int epi, const bf16_t *A, const bf16_t *W, void *C, int M, int 
         else gemm_reduce_kernel<EPI_F32_ROWMAJOR><<<g, 256, 0, st>>>(w4, slices, group, mn4, C);
         return false;
     }
-    if (M <= 512 && ((M + 127) / 128) * ((N + 63) / 64) <= cu_count()) {      // few rows, enough tiles for one round of them (QKV at a few hundred rows): 128x64 tiles, slices folded in registers
+    if (M <= 512 && ((M + 127) / 128) * ((N + 63) / 64) <= das_cu_count()) {      // few rows, enough tiles for one round of them (QKV at a few hundred rows): 128x64 tiles, slices folded in registers
         switch (epi) {
         case EPI_BF16_ROWMAJOR: launch_one<2, 2, 2, 1, 5, EPI_BF16_ROWMAJOR, 4, true, 1>(A, W, C, M, N, K, ldc, st, slice_tiles, slices, false, nullptr, 0.f, group); break;
         case EPI_RESID_F32: launch_one<2, 2, 2, 1, 5, EPI_RESID_F32, 4, true, 1>(A, W, C, M, N, K, ldc, st, slice_tiles, slices, false, nullptr, 0.f, group); break;
@@ -882,7 +882,7 @@ bool launch_gemm(int epi, const bf16_t *A, const bf16_t *W, void *C, int M, int 
     // Many rows: one workgroup per tile folds the slices in registers.  128x128 tiles (8 waves), or 192x128 (12 waves) when
     // that needs fewer rounds of workgroups times tile height: 1560 rows x 3584 columns are 364 tiles of 128 rows (two
     // rounds on 256 CUs) but 252 tiles of 192 rows (one round).
-    const int n_cu = cu_count();
+    const int n_cu = das_cu_count();
     const int tn = (N + 127) / 128;
     const long cost128 = (long)((((M + 127) / 128) * tn + n_cu - 1) / n_cu) * 128;
     const long cost192 = (long)((((M + 191) / 192) * tn + n_cu - 1) / n_cu) * 192;
