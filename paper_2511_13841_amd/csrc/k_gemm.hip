@@ -674,6 +674,23 @@ static int pick_tile_height(int M, int N, int lo) {
     return hb;
 }
 
+// Tile height (192 or 256 rows) of the two-halves-of-K shapes, 0 where tiles over all of K are expected to be faster: rounds of
+// workgroups times the time of a full round, measured on 3584 columns and K = 18944 (the RMSNorm that follows included, which the
+// halves shapes do in passing): 168 us for 192x192 halves, 215 for 256x192 halves, 198 for 128x128 and 277 for 192x128 over all
+// of K.  One round of halves wins wherever it fits (1088 rows 176 us against 173 + 10 of the norm, 1475 rows 222 against 250 + 10);
+// behind it 1537 .. 1728 rows are one round of 192x128 (260 + 10 against 300 us), 1792 and 2048 rows two rounds of 192x192
+// halves (315 against 330 + 11 us, 339 against 347 + 12), 3072 and 4096 rows two and three of 256x192 (446 against 535 + 18,
+// 630 against 741 + 24).
+static int pick_half_tiles(int M, int N) {
+    const long cus = das_cu_count();
+    auto rounds = [&](int th, int tw, int halves) { return ((long)((M + th - 1) / th) * ((N + tw - 1) / tw) * halves + cus - 1) / cus; };
+    if (rounds(192, 192, 2) == 1) return 192;
+    if (rounds(256, 192, 2) == 1) return 256;
+    const long t192 = 168 * rounds(192, 192, 2), t256 = 215 * rounds(256, 192, 2);
+    if (std::min(198 * rounds(128, 128, 1), 277 * rounds(192, 128, 1)) < std::min(t192, t256)) return 0;
+    return t192 <= t256 ? 192 : 256;
+}
+
 // A must be allocated for M rounded up to 256 rows plus another 256 (tiles of 96, 192 or 288 rows read past a multiple
 // of 256), W for N rounded up to 256 rows; K % 64 == 0.
 // EPI_ROWMAX needs N >= 16384 (the wide, one-pass shapes) and C = one zeroed 64-bit key per row.
@@ -814,15 +831,15 @@ bool launch_gemm(int epi, const bf16_t *A, const bf16_t *W, void *C, int M, int 
     }
     const size_t mn = (size_t)M * N;
     const int group = gemm_slice_group(slices);
-    const bool halves192 = ((M + 191) / 192) * ((N + 191) / 192) * 2 <= das_cu_count(), halves256 = ((M + 255) / 256) * ((N + 191) / 192) * 2 <= das_cu_count();
-    if (M > 512 && group > 0 && ws && ldc == N && (N % 4) == 0 && ws_floats >= 2 * mn && (halves192 || halves256)) {
+    const int halves = M > 512 && group > 0 ? pick_half_tiles(M, N) : 0;
+    if (halves > 0 && ws && ldc == N && (N % 4) == 0 && ws_floats >= 2 * mn) {
         // Many rows, long K (the down projection): 128x128 tiles over all of K move 32 KiB per k-tile of 64 and the launch
-        // runs at the speed of that copy stream.  When they fit the chip in one round, the two slice groups of the sum go to
+        // runs at the speed of that copy stream.  Where pick_half_tiles says so, the two slice groups of the sum go to
         // two workgroups instead, each with a tile of 192x192 over half of K: a quarter fewer bytes per multiply through
         // L2 -> LDS for the same number of workgroups; 4 waves (2 x 2) of 3x3 blocks (accumulators and the folded slices
-        // fill the register file), pipelined k loop, k-tiles of 32; with more rows a tile of 256x192 on 8 waves (4 x 2) of
+        // fill the register file), pipelined k loop, k-tiles of 32; or a tile of 256x192 on 8 waves (4 x 2) of
         // 2x3 blocks.  The kernel that adds the two halves also adds the residual and applies the RMSNorm that follows.
-        if (halves192) launch_one<2, 2, 3, 3, 6, EPI_F32_ROWMAJOR, 2, true, 3, true>(A, W, ws, M, N, K, N, st, 2 * slice_tiles, 2, false, nullptr, 0.f, group);
+        if (halves == 192) launch_one<2, 2, 3, 3, 6, EPI_F32_ROWMAJOR, 2, true, 3, true>(A, W, ws, M, N, K, N, st, 2 * slice_tiles, 2, false, nullptr, 0.f, group);
         else launch_one<4, 2, 2, 3, 5, EPI_F32_ROWMAJOR, 2, true, 3, true>(A, W, ws, M, N, K, N, st, 2 * slice_tiles, 2, false, nullptr, 0.f, group);
         if (epi == EPI_RESID_F32 && tail) {
             launch_reduce_resid_rmsnorm(ws, 2, 0, reinterpret_cast<float *>(C), tail->g, tail->y, M, N, tail->eps, st);
