@@ -15,7 +15,7 @@ def _prefill(shape, prompts, max_rows):
     import paper_2511_13841_amd as das
     lens = [len(p) for p in prompts]
     dm = das.DasModel(das.config_for(shape, max_seqs=len(prompts), max_ctx=max(lens) + 32, max_rows=max_rows, max_draft=0,
-                                     num_pages=sum(-(-n // 16) for n in lens) + 4), None, keep_logits=True, seed=3)
+                                     num_pages=sum(n // 16 + 1 for n in lens) + 4), None, keep_logits=True, seed=3)
     ids = list(range(len(prompts)))
     nxt = dm.prefill(ids, prompts)
     kv = [dm.kv_export(i, shape.n_layers - 1, 0, n) for i, n in zip(ids, lens)]
